@@ -100,7 +100,9 @@ __device__ __forceinline__ void subset_min(const R (&d2)[1 << MF], int b, R* m0,
 }
 
 // Exact LLR of bit b with every subset relative to its own smallest distance (whose term is 1:
-// a subset of one point needs no exponential, one of two points a single one).
+// a subset of one point needs no exponential, one of two points a single one).  Differences are
+// scaled in FP64 and rounded last: neither they nor c need lie in the FP32 range, and the smallest
+// distance's own term is 1 however large c times it is.
 template <int MF>
 __device__ __forceinline__ float subset_llr(const double (&d2)[1 << MF], int b, double c, double cnat) {
   double mn[2];
@@ -111,13 +113,12 @@ __device__ __forceinline__ float subset_llr(const double (&d2)[1 << MF], int b, 
 #pragma unroll
     for (int v = 0; v < 2; ++v) {
       const int p = v << b, o = p | (2 >> b);       // the subset's two points
-      s[v] = 1.0f + __builtin_amdgcn_exp2f(-fabsf(static_cast<float>(d2[p] - d2[o])) * static_cast<float>(c));
+      s[v] = 1.0f + __builtin_amdgcn_exp2f(static_cast<float>(-c * fabs(d2[p] - d2[o])));
     }
   } else {
-    const double cm[2] = {c * mn[0], c * mn[1]};
 #pragma unroll
     for (int p = 0; p < (1 << MF); ++p)
-      s[(p >> b) & 1] += __builtin_amdgcn_exp2f(static_cast<float>(fma(-c, d2[p], cm[(p >> b) & 1])));
+      s[(p >> b) & 1] += __builtin_amdgcn_exp2f(static_cast<float>(c * (mn[(p >> b) & 1] - d2[p])));
   }
   const float lg = kLn2f * (__builtin_amdgcn_logf(s[0]) - __builtin_amdgcn_logf(s[1]));
   return static_cast<float>(cnat * (mn[1] - mn[0]) + static_cast<double>(lg));

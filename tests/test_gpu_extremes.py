@@ -1,0 +1,82 @@
+"""Exact and max-log LLRs where FP32 squared distances, the noise's reciprocal or their product
+leave the FP32 range: constellations and noise scaled by 1e20 and 1e-20, noise far below the
+points' distances, and symbols at equal distance from several points.
+
+Tolerances.  Factors of up to four points, and constellations of up to 16: those of test_gpu_product.py
+for M <= 16, and 8 roundings of the farthest point's FP64 score, where scores cancel."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from test_gpu_product import shape
+
+pytestmark = pytest.mark.gpu
+
+DOUBLE = ["bpsk", "8psk", "gauss4", "gauss16", "qam4", "qam16", "2xqam16"]     # FP64 distances
+
+
+def md():
+    import paper_2104_06311_amd as m
+    return m
+
+
+def points(name):
+    if name == "gauss4":                                   # one factor of four points
+        return synth.gaussian_constellation(4, 2, 4)
+    return shape(name)
+
+
+def bound(name):
+    return 4e-6, 2.0 ** -23
+
+
+def received(X, s2, n, seed):
+    rng = np.random.default_rng(seed)
+    X64 = X.astype(np.float64)
+    y = X64[rng.integers(0, len(X), n)] + math.sqrt(s2) * rng.standard_normal((n, X.shape[1]))
+    y[0] = 0.0                                             # between the points of every axis
+    y[1] = X64[0]
+    y[2] = 0.5 * (X64[0] + X64[1])
+    y[3:6] *= 7.0                                          # outside the constellation
+    return y.astype(np.float32)
+
+
+def check_exact(X, labels, y, s2, atol, rtol):
+    Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    ld = torch.from_numpy(labels.astype(np.int32)).cuda()
+    want = oracle.llr_exact(X, labels, y, s2)
+    assert np.isfinite(want).all()
+    L = md().llr_exact(Xd, ld, yd, s2)
+    got = L.cpu().numpy().astype(np.float64)
+    far = ((y.astype(np.float64)[:, None] - X.astype(np.float64)) ** 2).sum(2).max(1, keepdims=True) / (2.0 * s2)
+    good = np.abs(got - want) <= atol + rtol * np.abs(want) + 8 * 2.0 ** -53 * far      # not where NaN
+    assert good.all(), (np.argwhere(~good)[:3], got[~good][:3], want[~good][:3])
+    tx = torch.zeros(len(y), dtype=torch.int32, device="cuda")
+    Lg, g, _ = md().llr_exact_gmi(Xd, ld, yd, tx, s2)
+    assert torch.equal(Lg, L) and torch.isfinite(g).all()
+    return Xd, ld, yd
+
+
+@pytest.mark.parametrize("name", DOUBLE)
+@pytest.mark.parametrize("scale", [1e20, 1e19, 1e-20])
+def test_scales(name, scale):
+    X, labels = points(name)
+    X = (X.astype(np.float64) * scale).astype(np.float32)
+    s2 = synth.sigma2_from_snr_db(X, 10.0)
+    y = received(X, s2, 517, 3)
+    Xd, ld, yd = check_exact(X, labels, y, s2, *bound(name))
+    got = md().llr_maxlog(Xd, ld, yd, s2).cpu().numpy().astype(np.float64)
+    want = oracle.llr_maxlog(X, labels, y, s2)
+    assert np.all(np.abs(got - want) <= 1e-9 + 2.0 ** -23 * np.abs(want))
+
+
+@pytest.mark.parametrize("name", DOUBLE)
+@pytest.mark.parametrize("snr_db", [60.0, 115.0, 200.0, 290.0])
+def test_little_noise(name, snr_db):
+    X, labels = points(name)
+    s2 = synth.sigma2_from_snr_db(X, snr_db)
+    check_exact(X, labels, received(X, s2, 517, 4), s2, *bound(name))
