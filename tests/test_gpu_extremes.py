@@ -80,3 +80,21 @@ def test_little_noise(name, snr_db):
     X, labels = points(name)
     s2 = synth.sigma2_from_snr_db(X, snr_db)
     check_exact(X, labels, received(X, s2, 517, 4), s2, *bound(name))
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_logarithms_of_small_constellations(seed):
+    """16 points of which some lie on the received value and the others out of reach: every subset's
+    sum is a whole number k of terms 1 and the LLR ln (k0 / k1), FP64 but for its last rounding
+    (and the 1e-10 that the logarithm's series leaves)."""
+    rng = np.random.default_rng(seed)
+    labels = np.arange(16, dtype=np.uint32)
+    near = rng.random(16) < 0.6
+    near[[0, 15]] = True                                   # no subset without one
+    X = np.where(near, 0.25, 1e4 + np.arange(16)).astype(np.float32)[:, None]
+    bits = (labels[:, None] >> np.arange(3, -1, -1)) & 1
+    k1 = (bits & near[:, None]).sum(0)
+    want = np.log((near.sum() - k1) / k1)
+    L = md().llr_exact(torch.from_numpy(X).cuda(), torch.from_numpy(labels.astype(np.int32)).cuda(),
+                       torch.full((3, 1), 0.25, device="cuda"), 0.5).cpu().numpy()
+    assert np.all(np.abs(L - want) <= 2.0 ** -24 * np.abs(want) + 2e-10), (L[0], want)
