@@ -15,8 +15,9 @@
 //   exact, 8 and 16 points of M >= 32 (where the general path's scores are FP32): FP32
 //     distances, one exponential per point relative to the nearest, the subset sums by a tree,
 //     L_b = ln (S0 / S1).  A bit whose smaller sum fell below 2^-100 takes its subsets' smallest
-//     distances in FP64 and their sums relative to them; a symbol far from every point (256
-//     base-2 units, where FP32 distances lose the points' differences) the FP64 form throughout.
+//     distances in FP64 and their sums relative to them.  A symbol whose distances reach too far
+//     for that (in_range) takes the FP64 form for every factor, and so does every symbol of a call whose
+//     c or points are outside the FP32 form's range (all_symbols).
 // A non-finite received value gives NaN LLRs, as on the general path.
 //
 // Bound by memory for up to 4 points a factor (4e6 symbols of 16-QAM, a whole call: 207.7 ->
@@ -153,8 +154,8 @@ __device__ __forceinline__ float subset_llr(const double (&d2)[1 << MF], int b, 
   return static_cast<float>(fma(cnat, mn[1] - mn[0], lg));
 }
 
-// The exact LLR of bit b in FP64 for the few far symbols of the FP32 form, point by point (no
-// array: it shares that form's registers).
+// The exact LLR of bit b in FP64 distances for symbols that the FP32 form does not take, point by
+// point (no array: it shares that form's registers).
 __device__ __forceinline__ float far_llr(const ProdTables& T, const float* __restrict__ row, int mf, int b, double c,
                                          double cnat) {
   const int df = T.fd[1];
@@ -194,30 +195,39 @@ constexpr bool kFloat = MODE == PROD_FLOAT && MF >= 3;
 template <int MODE, int MF>
 using Real = typename std::conditional<kFloat<MODE, MF>, float, double>::type;
 
+// How far a symbol's factors reach, in base-2 units: the sum of their nearest points' scores, and the
+// largest distance from there to a subset's best point (counted where a sum fell below 2^-100).
+struct Reach {
+  float top = 0.0f, beyond = 0.0f;
+};
+// FP32 distances carry 3 roundings of their score, which must stay small beside 1 for the nearest
+// points; and beyond 575 units the general path's FP32 windows end as well.  Not for NaN or infinity.
+__device__ __forceinline__ bool in_range(const Reach& r) { return r.top <= 256.0f && r.top + r.beyond <= 575.0f; }
+
 // The LLR of bit b when one of its sums is too small: FP64 smallest distances (dist64(p): the
 // distance of point p), FP32 sums relative to the FP32 ones.
 template <int MF, class F>
-__device__ __forceinline__ float wide_llr(const float (&d2)[1 << MF], int b, float cf, double cnat, F dist64) {
+__device__ __forceinline__ float wide_llr(const float (&d2)[1 << MF], int b, float cf, double cnat, F dist64, float top,
+                                          Reach& reach) {
   float mf[2];
   subset_min<MF>(d2, b, &mf[0], &mf[1]);
-  const float cm[2] = {cf * mf[0], cf * mf[1]};
+  reach.beyond = fmaxf(reach.beyond, cf * fmaxf(mf[0], mf[1]) - top);
   double mn[2] = {INFINITY, INFINITY};
   float s[2] = {0.0f, 0.0f};
 #pragma unroll
   for (int p = 0; p < (1 << MF); ++p) {
     const int v = (p >> b) & 1;
     mn[v] = fmin(mn[v], dist64(p));
-    s[v] += __builtin_amdgcn_exp2f(fmaf(-cf, d2[p], cm[v]));
+    s[v] += __builtin_amdgcn_exp2f(cf * (mf[v] - d2[p]));
   }
   const float lg = kLn2f * (__builtin_amdgcn_logf(s[0]) - __builtin_amdgcn_logf(s[1]));
   return static_cast<float>(cnat * (mn[1] - mn[0]) + static_cast<double>(lg));
 }
 
-// The LLRs of a factor's bits from its squared distances (LOG64: see subset_llr).  Returns whether they are good (false:
-// a far symbol, see above).
+// The LLRs of a factor's bits from its squared distances (LOG64: see subset_llr).
 template <int MODE, int MF, bool LOG64, class F>
-__device__ __forceinline__ bool llr_from_distances(const Real<MODE, MF> (&d2)[1 << MF], double c, double cnat,
-                                                   float (&L)[MF], F dist64) {
+__device__ __forceinline__ void llr_from_distances(const Real<MODE, MF> (&d2)[1 << MF], double c, double cnat,
+                                                   float (&L)[MF], F dist64, Reach& reach) {
   constexpr int MP = 1 << MF;
   if constexpr (MODE == PROD_MAXLOG) {
 #pragma unroll
@@ -226,14 +236,12 @@ __device__ __forceinline__ bool llr_from_distances(const Real<MODE, MF> (&d2)[1 
       subset_min<MF>(d2, b, &m0, &m1);
       L[b] = static_cast<float>(cnat * (m1 - m0));
     }
-    return true;
   } else if constexpr (!kFloat<MODE, MF>) {
 #pragma unroll
     for (int b = 0; b < MF; ++b) {
       L[b] = subset_llr<MF, LOG64>(d2, b, c, cnat);
       __builtin_amdgcn_sched_barrier(0);       // one bit's temporaries at a time (registers)
     }
-    return true;
   } else {
     const float cf = static_cast<float>(c);
     float dmin = d2[0];
@@ -255,11 +263,11 @@ __device__ __forceinline__ bool llr_from_distances(const Real<MODE, MF> (&d2)[1 
         a1 += v[k + 1];
       }
       L[b] = fminf(a0, a1) >= 0x1p-100f ? kLn2f * __builtin_amdgcn_logf(a0 * __builtin_amdgcn_rcpf(a1))
-                                        : wide_llr<MF>(d2, b, cf, cnat, dist64);
+                                        : wide_llr<MF>(d2, b, cf, cnat, dist64, top, reach);
 #pragma unroll
       for (int k = 0; k < cnt / 2; ++k) v[k] = v[2 * k] + v[2 * k + 1];
     }
-    return top <= 256.0f;
+    reach.top += top;
   }
 }
 
@@ -288,10 +296,31 @@ __device__ __forceinline__ float loss_of(const float (&L)[MF], ConstInt* fd, int
   return t;
 }
 
+// All factors of a symbol by the FP64 form; returns the sum of their loss terms.
+template <bool GMI>
+__device__ __forceinline__ float far_symbol(ProdTables T, ConstInt* head, const float* __restrict__ row, int m, double c,
+                                            double cnat, float* __restrict__ lrow, uint32_t lab) {
+  const int nf = head[0];
+  float term = 0.0f;
+#pragma unroll 1
+  for (int f = 0; f < nf; ++f) {
+    T.fd = head + kProdHead + kProdFactor * f;
+    const int mf = T.fd[0];
+#pragma unroll 1
+    for (int b = 0; b < mf; ++b) {
+      const float L = far_llr(T, row, mf, b, c, cnat);
+      const int k = T.fd[3 + b];
+      lrow[k] = L;
+      if constexpr (GMI) term += softplus_bits(((lab >> (m - 1 - k)) & 1u) ? L : -L);
+    }
+  }
+  return term;
+}
+
 // One factor of a symbol, any shape.
 template <int MODE, int MF, bool GMI>
 __device__ __forceinline__ float factor_llr(const ProdTables& T, const float* __restrict__ row, int m, double c, double cnat,
-                                            float* __restrict__ lrow, uint32_t lab, float* nonfinite) {
+                                            float* __restrict__ lrow, uint32_t lab, float* nonfinite, Reach& reach) {
   Real<MODE, MF> d2[1 << MF];
   distances<MF>(T, row, d2, nonfinite);
   float L[MF];
@@ -304,10 +333,7 @@ __device__ __forceinline__ float factor_llr(const ProdTables& T, const float* __
     }
     return r;
   };
-  if (!llr_from_distances<MODE, MF, MODE == PROD_DOUBLE>(d2, c, cnat, L, dist64)) {
-#pragma unroll
-    for (int b = 0; b < MF; ++b) L[b] = far_llr(T, row, MF, b, c, cnat);
-  }
+  llr_from_distances<MODE, MF, MODE == PROD_DOUBLE>(d2, c, cnat, L, dist64, reach);
   store_llrs<MF>(L, T.fd, T.fd[7] != 0, T.fd[2 + MF], lrow);
   return GMI ? loss_of<MF>(L, T.fd, m, lab) : 0.0f;
 }
@@ -328,6 +354,7 @@ struct SymbolArgs {
   int m, D;
   double c, cnat;
   float start;            // 0, or NaN when the labels are broken
+  bool fp32_ok;           // the FP32 form may be used
 };
 
 template <bool GMI>
@@ -388,6 +415,8 @@ __device__ __forceinline__ void fixed_symbols(const ProdTables& T0, ConstInt* he
 #pragma unroll
     for (int d = 0; d < DT; ++d) nonfinite = fmaf(yv[d], 0.0f, nonfinite);
     const uint32_t lab = sent_label<GMI>(A, n, &term);
+    const float none = term;
+    Reach reach;
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
       R d2[MP];
@@ -411,15 +440,12 @@ __device__ __forceinline__ void fixed_symbols(const ProdTables& T0, ConstInt* he
         return r;
       };
       constexpr bool log64 = MODE == PROD_DOUBLE && (NF == 1 || MF > 2);
-      if (!llr_from_distances<MODE, MF, log64>(d2, A.c, A.cnat, L, dist64)) {
-        ProdTables T = T0;
-        T.fd = fd[f];
-#pragma unroll
-        for (int b = 0; b < MF; ++b) L[b] = far_llr(T, A.y + n * DT, MF, b, A.c, A.cnat);
-      }
+      llr_from_distances<MODE, MF, log64>(d2, A.c, A.cnat, L, dist64, reach);
       store_llrs<MF>(L, fd[f], run, last[f], A.llr + n * A.m);
       if constexpr (GMI) term += loss_of<MF>(L, fd[f], A.m, lab);
     }
+    if (MODE == PROD_FLOAT && !(A.fp32_ok && in_range(reach)))
+      term = none + far_symbol<GMI>(T0, head, A.y + n * DT, A.m, A.c, A.cnat, A.llr + n * A.m, lab);
     finish_symbol<GMI>(A, n, nonfinite, term);
   }
 }
@@ -442,6 +468,10 @@ template <int MODE, bool GMI, int DT>
 __device__ __forceinline__ void all_symbols(const ProdArgs& G, const int* __restrict__ flags, SymbolArgs A) {
   ConstInt* fl = reinterpret_cast<ConstInt*>(reinterpret_cast<uint64_t>(flags));
   A.start = fl[0] != 0 ? __builtin_nanf("") : 0.0f;
+  // The FP32 form: while an FP32 squared distance that overflows means a score of 2^28 and more, and
+  // one that underflows a score below 2^-28; and not for constellations the general path would
+  // leave to its FP64 kernel (flags[2]).
+  A.fp32_ok = A.c >= 1e-30 && A.c <= 1e30 && fl[2] == 0;
   ConstInt* head = reinterpret_cast<ConstInt*>(reinterpret_cast<uint64_t>(G.prod));
   ProdTables T;
   T.td = reinterpret_cast<ConstDouble*>(reinterpret_cast<uint64_t>(G.ptab));
@@ -467,16 +497,20 @@ __device__ __forceinline__ void all_symbols(const ProdArgs& G, const int* __rest
     float* lrow = A.llr + n * A.m;
     float nonfinite = A.start, term = 0.0f;
     const uint32_t lab = sent_label<GMI>(A, n, &term);
+    const float none = term;
+    Reach reach;
     for (int i = 0; i < nconst; ++i) nonfinite = fmaf(row[head[2 + i]], 0.0f, nonfinite);
     for (int f = 0; f < nf; ++f) {
       T.fd = head + kProdHead + kProdFactor * f;
       switch (T.fd[0]) {
-        case 1: term += factor_llr<MODE, 1, GMI>(T, row, A.m, A.c, A.cnat, lrow, lab, &nonfinite); break;
-        case 2: term += factor_llr<MODE, 2, GMI>(T, row, A.m, A.c, A.cnat, lrow, lab, &nonfinite); break;
-        case 3: term += factor_llr<MODE, 3, GMI>(T, row, A.m, A.c, A.cnat, lrow, lab, &nonfinite); break;
-        default: term += factor_llr<MODE, 4, GMI>(T, row, A.m, A.c, A.cnat, lrow, lab, &nonfinite); break;
+        case 1: term += factor_llr<MODE, 1, GMI>(T, row, A.m, A.c, A.cnat, lrow, lab, &nonfinite, reach); break;
+        case 2: term += factor_llr<MODE, 2, GMI>(T, row, A.m, A.c, A.cnat, lrow, lab, &nonfinite, reach); break;
+        case 3: term += factor_llr<MODE, 3, GMI>(T, row, A.m, A.c, A.cnat, lrow, lab, &nonfinite, reach); break;
+        default: term += factor_llr<MODE, 4, GMI>(T, row, A.m, A.c, A.cnat, lrow, lab, &nonfinite, reach); break;
       }
     }
+    if (MODE == PROD_FLOAT && !(A.fp32_ok && in_range(reach)))
+      term = none + far_symbol<GMI>(T, head, row, A.m, A.c, A.cnat, lrow, lab);
     finish_symbol<GMI>(A, n, nonfinite, term);
   }
 }
@@ -496,6 +530,7 @@ inline SymbolArgs symbol_args(const Prepared& P, int M, int D, const float* d_y,
   A.cnat = 1.0 / (2.0 * sigma2);
   A.c = A.cnat * 1.4426950408889634;
   A.start = 0.0f;
+  A.fp32_ok = true;
   return A;
 }
 

@@ -3,7 +3,8 @@ leave the FP32 range: constellations and noise scaled by 1e20 and 1e-20, noise f
 points' distances, and symbols at equal distance from several points.
 
 Tolerances.  Factors of up to four points, and constellations of up to 16: those of test_gpu_product.py
-for M <= 16, and 8 roundings of the farthest point's FP64 score, where scores cancel."""
+for M <= 16; other products: those of its FP32 distances; and 8 roundings of the farthest point's
+FP64 score, where scores cancel."""
 import math
 
 import numpy as np
@@ -12,11 +13,12 @@ import torch
 
 import oracle
 import synth
-from test_gpu_product import shape
+from test_gpu_product import pam, product, shape
 
 pytestmark = pytest.mark.gpu
 
 DOUBLE = ["bpsk", "8psk", "gauss4", "gauss16", "qam4", "qam16", "2xqam16"]     # FP64 distances
+SINGLE = ["qam64", "qam256", "psk8x2", "rect32", "three", "planes256", "flat64", "quarter64"]   # some FP32
 
 
 def md():
@@ -27,11 +29,15 @@ def md():
 def points(name):
     if name == "gauss4":                                   # one factor of four points
         return synth.gaussian_constellation(4, 2, 4)
+    if name == "quarter64":                                # factors of four and of sixteen points
+        return product(pam(4), pam(16))
     return shape(name)
 
 
 def bound(name):
-    return 4e-6, 2.0 ** -23
+    if name in DOUBLE:
+        return 4e-6, 2.0 ** -23
+    return 3 * 2.0 ** -24 * 256 * math.log(2.0) + 4e-6, 4 * 2.0 ** -24
 
 
 def received(X, s2, n, seed):
@@ -61,7 +67,7 @@ def check_exact(X, labels, y, s2, atol, rtol):
     return Xd, ld, yd
 
 
-@pytest.mark.parametrize("name", DOUBLE)
+@pytest.mark.parametrize("name", DOUBLE + SINGLE)
 @pytest.mark.parametrize("scale", [1e20, 1e19, 1e-20])
 def test_scales(name, scale):
     X, labels = points(name)
@@ -74,8 +80,8 @@ def test_scales(name, scale):
     assert np.all(np.abs(got - want) <= 1e-9 + 2.0 ** -23 * np.abs(want))
 
 
-@pytest.mark.parametrize("name", DOUBLE)
-@pytest.mark.parametrize("snr_db", [60.0, 115.0, 200.0, 290.0])
+@pytest.mark.parametrize("name", DOUBLE + SINGLE)
+@pytest.mark.parametrize("snr_db", [60.0, 100.0, 115.0, 200.0, 290.0])
 def test_little_noise(name, snr_db):
     X, labels = points(name)
     s2 = synth.sigma2_from_snr_db(X, snr_db)
