@@ -118,8 +118,8 @@ struct Prepared {
   const uint4* frag;        // MFMA A-operand fragments (see prep.hip)
   int* flags;               // [0] labels invalid, [1] first fallback count, [2] constellation
                             // outside the FP16 split range, [3] second fallback count,
-                            // [4] third fallback count, [5] the product kernel takes the call
-                            // (8 ints)
+                            // [4] third fallback count, [5] the product kernel takes the call,
+                            // [6] it left symbols (8 ints)
   unsigned* fb_list;        // symbols the fast pass could not finish (capacity N); after the
                             // second pass it is reused for the third list (careful kernel)
   unsigned* fb_list2;       // symbols left after the two-window pass (capacity N)

@@ -39,6 +39,7 @@
 
 #include "common.hpp"
 #include "llr_kernels.hpp"
+#include "llr_prod.hpp"
 
 namespace md {
 
@@ -74,8 +75,10 @@ __device__ __forceinline__ double wave_sum(double v) {
 //            g + ln(sum).  A smaller sum means the subset lies more than ~667 nats below
 //            g: it is summed again against its own maximum (in practice never).
 //   max-log: pass 1 alone, with max in place of the sums.
-// Used for the symbols the fast passes hand over (M >= 32).
+// Used for the symbols the fast passes hand over (M >= 32), and for those the product kernel marks
+// (prodk::rest_columns).
 constexpr int kCarefulWaves = 4;
+static_assert(kCarefulWaves * 64 == prodk::kProdThreads);
 constexpr int kChunkPts = 512;                 // 512 rows of at most 31 floats: <= 62 KiB of LDS
 constexpr int kChunkBits = 9;
 constexpr int kMaxHigh = kMaxM - kChunkBits;   // label bits routed by chunk index
@@ -125,8 +128,13 @@ __global__ void __launch_bounds__(kCarefulWaves * 64) llr_careful_kernel(const f
                                                                          double cnat, float* __restrict__ llr,
                                                                          const int* __restrict__ flags,
                                                                          const unsigned* __restrict__ list,
-                                                                         int count_slot) {
+                                                                         int count_slot, prodk::ProdArgs G,
+                                                                         prodk::SymbolArgs A, int masks) {
   extern __shared__ float pts[];                 // kChunkPts rows of Dp floats
+  if constexpr (!MAXLOG) {
+    __shared__ prodk::RestList left;
+    if (flags[5]) return prodk::rest_columns(G, A, masks, left);   // the product kernel took the call
+  }
   const int Dp = D | 1;                          // odd row stride: no LDS bank conflicts
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t count = list ? static_cast<int64_t>(flags[count_slot]) : N;
@@ -252,7 +260,8 @@ int launch_careful_t(const Prepared& P, int M, int D, const float* d_y, int64_t 
   const double cnat = 1.0 / (2.0 * sigma2);
   const size_t lds = sizeof(float) * static_cast<size_t>(kChunkPts) * (D | 1);
   hipLaunchKernelGGL(llr_careful_kernel<MAXLOG>, dim3(static_cast<unsigned>(grid)), dim3(kCarefulWaves * 64), lds,
-                     stream, P.xl, M, m, D, d_y, N, cnat, d_llr, P.flags, list, count_slot);
+                     stream, P.xl, M, m, D, d_y, N, cnat, d_llr, P.flags, list, count_slot, prodk::prod_args(P),
+                     prodk::symbol_args(P, M, D, d_y, N, sigma2, d_llr), prodk::rest_masks((N + 63) / 64, grid));
   MD_LAUNCH_CHECK("llr_careful_kernel launch");
   return MD_OK;
 }

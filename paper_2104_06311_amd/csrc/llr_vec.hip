@@ -137,7 +137,7 @@ __global__ void __launch_bounds__(kVecThreads) llr_vec_kernel(const float* __res
 // The symbols the kernel above left (exact LLRs out of the FP32 range), four lanes each: lane q takes
 // the M / 4 labels from q M / 4 on, so the two high label bits are the lane and the rest its position.
 // A block takes chunks of up to 1024 symbols and lists the marked ones in LDS, where the points are
-// too.  Every point's score relative to the best one is -c (d2 - dmin) = k + f in FP64, k an integer
+// too.  (Products: prodk::rest_columns.)  Every point's score relative to the best one is -c (d2 - dmin) = k + f in FP64, k an integer
 // and |f| <= 1/2; the exponential of f is FP32 and k stays an integer, so a subset's sum is taken
 // relative to its own largest k and no range is lost: M exponentials a symbol, and five plain
 // operations per point and bit.  Scores saturate 2^30 below the best: a subset that far has its
@@ -149,8 +149,6 @@ __global__ void __launch_bounds__(kVecThreads) llr_vec_kernel(const float* __res
 // and 260 us where all of 1e6 are, four take 18.8 and 185.  Whole calls at M = 64, 4D Gaussian,
 // before -> now: 2000 symbols 27.7 -> 16.4 us, all of them out of range 67 -> 18.8; 1e6 symbols
 // 38.3 -> 33.5, a tenth out of range 209 -> 58, all 13266 -> 185.
-constexpr int kRestMasks = 16;                 // 64-symbol masks of the largest chunk
-
 template <int XOR>
 __device__ __forceinline__ int quad_xor(int v) {
   return __builtin_amdgcn_update_dpp(0, v, XOR == 1 ? 0xB1 : 0x4E, 0xf, 0xf, true);
@@ -265,40 +263,24 @@ template <int MB, int D>
 __global__ void __launch_bounds__(kVecThreads) llr_vec_rest_kernel(const float* __restrict__ xl_g,
                                                                    const float* __restrict__ y, int64_t N, double cnat,
                                                                    float* __restrict__ llr, int* __restrict__ flags,
-                                                                   const uint64_t* __restrict__ left, int masks) {
+                                                                   const uint64_t* __restrict__ left, int masks,
+                                                                   prodk::ProdArgs G, prodk::SymbolArgs A) {
   constexpr int kRun = (1 << MB) / 4 * D, kStep = kRun + 4;   // the four runs of points in other LDS banks
   __shared__ float pts[4 * kStep];
-  __shared__ unsigned short list[kRestMasks * 64];
-  __shared__ int count_sh;
-  if (flags[5]) return;
+  __shared__ prodk::RestList list;
+  if (flags[5]) return prodk::rest_columns(G, A, masks, list);
   for (int i = threadIdx.x; i < 4 * kRun; i += kVecThreads) pts[i / kRun * kStep + i % kRun] = xl_g[i];
   const int64_t nmask = (N + 63) / 64;
   const double c = cnat * 1.4426950408889634;
   const int q = threadIdx.x & 3;
   for (int64_t m0 = static_cast<int64_t>(blockIdx.x) * masks; m0 < nmask;
        m0 += static_cast<int64_t>(gridDim.x) * masks) {
-    // wavefront 0: one mask per lane, places by a prefix sum
-    if (threadIdx.x < 64) {
-      uint64_t mk = (static_cast<int>(threadIdx.x) < masks && m0 + threadIdx.x < nmask) ? left[m0 + threadIdx.x] : 0;
-      const int own = __popcll(mk);
-      int at = own;
-#pragma unroll
-      for (int o = 1; o < kRestMasks; o <<= 1) {
-        const int up = __shfl_up(at, o, 64);
-        if (static_cast<int>(threadIdx.x) >= o) at += up;
-      }
-      if (threadIdx.x == kRestMasks - 1) {
-        count_sh = at;
-        if (at) atomicAdd(&flags[1], at);
-      }
-      at -= own;
-      for (; mk; mk &= mk - 1)
-        list[at++] = static_cast<unsigned short>(64 * threadIdx.x + __ffsll(static_cast<unsigned long long>(mk)) - 1);
-    }
+    prodk::list_left(left, m0, nmask, masks, list);
     __syncthreads();
-    const int count = count_sh;
+    const int count = list.count;
+    if (threadIdx.x == 0 && count) atomicAdd(&flags[1], count);
     for (int i = threadIdx.x / 4; i < count; i += kVecThreads / 4)
-      rest_symbol<MB, D>(pts + q * kStep, q, y, 64 * m0 + list[i], c, cnat, llr);
+      rest_symbol<MB, D>(pts + q * kStep, q, y, 64 * m0 + list.item[i], c, cnat, llr);
     __syncthreads();
   }
 }
@@ -323,13 +305,12 @@ int launch_vec_g(const Prepared& P, const float* d_y, int64_t N, double sigma2, 
   if constexpr (MAXLOG) return MD_OK;         // scores never leave the range
   // four blocks per compute unit, then chunks of more than one mask
   const int64_t nmask = (N + 63) / 64;
-  int64_t masks = (nmask + 4 * ncu - 1) / (4 * ncu);
-  if (masks > kRestMasks) masks = kRestMasks;
+  const int masks = prodk::rest_masks(nmask, 4 * ncu);
   int64_t rest = (nmask + masks - 1) / masks;
   if (rest > 4 * ncu) rest = 4 * ncu;
   hipLaunchKernelGGL((llr_vec_rest_kernel<MB, D>), dim3(static_cast<unsigned>(rest)), dim3(kVecThreads), 0, stream,
                      P.xl, d_y, N, 1.0 / (2.0 * sigma2), d_llr, P.flags, reinterpret_cast<const uint64_t*>(P.fb_list),
-                     static_cast<int>(masks));
+                     masks, prodk::prod_args(P), prodk::symbol_args(P, 1 << MB, D, d_y, N, sigma2, d_llr));
   MD_LAUNCH_CHECK("llr_vec_rest_kernel launch");
   return MD_OK;
 }

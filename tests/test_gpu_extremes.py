@@ -104,3 +104,30 @@ def test_logarithms_of_small_constellations(seed):
     L = md().llr_exact(torch.from_numpy(X).cuda(), torch.from_numpy(labels.astype(np.int32)).cuda(),
                        torch.full((3, 1), 0.25, device="cuda"), 0.5).cpu().numpy()
     assert np.all(np.abs(L - want) <= 2.0 ** -24 * np.abs(want) + 2e-10), (L[0], want)
+
+
+def coinciding(n, seed):
+    """n points of which some lie at 0.25, in both halves of every bit, and the others out of reach."""
+    near = np.random.default_rng(seed).random(n) < 0.6
+    near[[0, n - 1]] = True
+    return np.where(near, 0.25, 1e4 + np.arange(n)), near
+
+
+@pytest.mark.parametrize("other", [2, 4, 8, 16])
+@pytest.mark.parametrize("n", [8, 16])
+@pytest.mark.parametrize("seed", range(3))
+def test_far_symbols_are_demapped_in_fp64(n, other, seed):
+    """As above, in a product whose other factor's points are out of the FP32 sums' reach: ln (k0 / k1)
+    but for the last rounding (2e-12: FP64 exponentials and logarithms)."""
+    if n * other < 32:
+        pytest.skip("M <= 16 has FP32 sums")
+    x, near = coinciding(n, seed)
+    X, labels = product((x, np.arange(n)), (1e3 * np.arange(other), np.arange(other)))
+    mf = n.bit_length() - 1
+    bits = (np.arange(n)[:, None] >> np.arange(mf - 1, -1, -1)) & 1
+    k1 = (bits & near[:, None]).sum(0)
+    want = np.log((near.sum() - k1) / k1)
+    L = md().llr_exact(torch.from_numpy(X).cuda(), torch.from_numpy(labels.astype(np.int32)).cuda(),
+                       torch.tensor([[0.25, 0.0], [0.25, 1e3]], device="cuda"), 0.5)
+    assert md().llr_path_counts() == (0, 0)
+    assert np.all(np.abs(L.cpu().numpy()[:, :mf] - want) <= 2.0 ** -24 * np.abs(want) + 2e-12), (L[:, :mf], want)
