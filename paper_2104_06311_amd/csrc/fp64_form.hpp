@@ -26,13 +26,23 @@ __device__ __forceinline__ double exp2_fraction(double f) {
   return fma(p, f, 1.0);
 }
 
-// 2^-r for r >= 0 (0 beyond the FP64 range; NaN for NaN).
-__device__ __forceinline__ double exp2_neg(double r) {
+// 2^-r, r >= 0, as 2^k e with an integer k and e in [2^-1/2, 2^1/2], so that sums can be taken relative to
+// any of their terms; k saturates at -2^30.  e is NaN for NaN.
+constexpr double kFar = 1073741824.0;
+__device__ __forceinline__ bool saturated(int k) { return k < -1073741820; }
+__device__ __forceinline__ void exp2_neg(double r, int* k, double* e) {
   constexpr double kMagic = 6755399441055744.0;           // 1.5 * 2^52: an integer in the low word
-  const double t = r > 2000.0 ? -2000.0 : -r;
+  const double t = r > kFar ? -kFar : -r;
   const double s = t + kMagic;
-  const int k = static_cast<int>(static_cast<uint32_t>(__builtin_bit_cast(uint64_t, s)));
-  return ldexp(exp2_fraction(t - (s - kMagic)), k);
+  *k = static_cast<int>(static_cast<uint32_t>(__builtin_bit_cast(uint64_t, s)));
+  *e = exp2_fraction(t - (s - kMagic));
+}
+// 2^-r itself (0 beyond the FP64 range).
+__device__ __forceinline__ double exp2_neg(double r) {
+  int k;
+  double e;
+  exp2_neg(r, &k, &e);
+  return ldexp(e, k);
 }
 
 // ln (a / b) of two positive FP64 numbers by `TERMS` terms of 2 artanh(z), z = (a - b) / (a + b), with

@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "fp64_form.hpp"
 #include "llr_fast.hpp"
 #include "llr_kernels.hpp"
 #include "llr_prod.hpp"
@@ -137,42 +138,40 @@ __global__ void __launch_bounds__(kVecThreads) llr_vec_kernel(const float* __res
 // The symbols the kernel above left (exact LLRs out of the FP32 range), four lanes each: lane q takes
 // the M / 4 labels from q M / 4 on, so the two high label bits are the lane and the rest its position.
 // A block takes chunks of up to 1024 symbols and lists the marked ones in LDS, where the points are
-// too.  (Products: prodk::rest_columns.)  Every point's score relative to the best one is -c (d2 - dmin) = k + f in FP64, k an integer
-// and |f| <= 1/2; the exponential of f is FP32 and k stays an integer, so a subset's sum is taken
-// relative to its own largest k and no range is lost: M exponentials a symbol, and five plain
-// operations per point and bit.  Scores saturate 2^30 below the best: a subset that far has its
-// smallest distance alone (its sum moves the LLR by ln M at most, of 7e8).
+// too.  (Products: prodk::rest_columns.)  Distances, exponentials, sums and logarithms are FP64, as in the
+// kernel for such symbols of larger constellations; every point's score relative to the best one is
+// 2^k e (fp64_form.hpp), so a subset's sum is taken relative to its own largest term and no range is lost:
+// M exponentials a symbol.  Scores saturate 2^30 below the best: a subset that far has its smallest
+// distance alone (its sum moves the LLR by ln M at most, of 7e8).
 // One launch in place of the matrix-core path's three later passes (two and three exponent windows,
-// FP64).  What bounds it is the FP64 and integer arithmetic of the listed symbols, and a call of a
-// few thousand symbols waits for one symbol's chain: four lanes, because one lane a symbol (the
-// distances formed twice to save registers) took 82 us where all of 2000 symbols are out of range
-// and 260 us where all of 1e6 are, four take 18.8 and 185.  Whole calls at M = 64, 4D Gaussian,
-// before -> now: 2000 symbols 27.7 -> 16.4 us, all of them out of range 67 -> 18.8; 1e6 symbols
-// 38.3 -> 33.5, a tenth out of range 209 -> 58, all 13266 -> 185.
+// FP64).  What bounds it is the FP64 arithmetic of the listed symbols, and a call of a few thousand
+// symbols waits for one symbol's chain: one lane a symbol (the distances formed twice to save
+// registers) took 82 us where all of 2000 symbols are out of range and 260 us where all of 1e6 are, four
+// 18.8 and 185, with FP32 exponentials.  FP64 ones are no slower at M = 64 since the points are read from
+// LDS for every symbol (kept in registers they left one wavefront a SIMD): all of 2e6 symbols of 64 4D
+// points 352 -> 310 us a call, 64 8D 418 -> 377; 32 2D points, whose registers sufficed, 141 -> 174.
+// Whole calls at M = 64, 4D, by the three later passes -> now: 2000 symbols all out of range 66 -> 18 us, 2e6
+// symbols 1.7 % out of range 264 -> 78, all 33100 -> 310.
 template <int XOR>
 __device__ __forceinline__ int quad_xor(int v) {
   return __builtin_amdgcn_update_dpp(0, v, XOR == 1 ? 0xB1 : 0x4E, 0xf, 0xf, true);
 }
 template <int XOR>
-__device__ __forceinline__ float quad_xor(float v) {
-  return __builtin_bit_cast(float, quad_xor<XOR>(__builtin_bit_cast(int, v)));
+__device__ __forceinline__ double quad_xor(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = static_cast<uint32_t>(quad_xor<XOR>(static_cast<int>(static_cast<uint32_t>(u))));
+  const uint32_t hi = static_cast<uint32_t>(quad_xor<XOR>(static_cast<int>(static_cast<uint32_t>(u >> 32))));
+  return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
 }
 __device__ __forceinline__ double quad_min(double v) {
-  auto other = [&](auto x) {
-    constexpr int X = decltype(x)::value;
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = static_cast<uint32_t>(quad_xor<X>(static_cast<int>(static_cast<uint32_t>(u))));
-    const uint32_t hi = static_cast<uint32_t>(quad_xor<X>(static_cast<int>(static_cast<uint32_t>(u >> 32))));
-    return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
-  };
-  v = fmin(v, other(std::integral_constant<int, 1>{}));
-  return fmin(v, other(std::integral_constant<int, 2>{}));
+  v = fmin(v, quad_xor<1>(v));
+  return fmin(v, quad_xor<2>(v));
 }
 __device__ __forceinline__ int quad_max(int v) {
   v = max(v, quad_xor<1>(v));
   return max(v, quad_xor<2>(v));
 }
-__device__ __forceinline__ float quad_sum(float v) {
+__device__ __forceinline__ double quad_sum(double v) {
   v += quad_xor<1>(v);
   return v + quad_xor<2>(v);
 }
@@ -194,32 +193,36 @@ __device__ __forceinline__ void rest_symbol(const float* x, int q, const float* 
     }
     return d2;
   };
-  double d2[P];
-  double dmin = INFINITY;
-#pragma unroll
-  for (int i = 0; i < P; ++i) {
-    d2[i] = dist(i);
-    dmin = fmin(dmin, d2[i]);
-  }
-  dmin = quad_min(dmin);
-  constexpr double kMagic = 6755399441055744.0;           // 1.5 * 2^52: an integer in the low word
-  constexpr double kFar = 1073741824.0;
-  float e[P];
+  double e[P];
   int k[P];
+  {
+    double d2[P];
+    double dmin = INFINITY;
 #pragma unroll
-  for (int i = 0; i < P; ++i) {
-    const double r = c * (d2[i] - dmin);                  // NaN for a received value that is not finite
-    const double t = r > kFar ? -kFar : -r;
-    const double s = t + kMagic;
-    k[i] = static_cast<int>(static_cast<uint32_t>(__builtin_bit_cast(uint64_t, s)));
-    e[i] = __builtin_amdgcn_exp2f(static_cast<float>(t - (s - kMagic)));
+    for (int i = 0; i < P; ++i) {
+      d2[i] = dist(i);
+      dmin = fmin(dmin, d2[i]);
+    }
+    dmin = quad_min(dmin);
+#pragma unroll
+    for (int i = 0; i < P; ++i) fp64::exp2_neg(c * (d2[i] - dmin), &k[i], &e[i]);
+  }
+  // lane q finishes the bits b = q mod 4
+  constexpr int R = (MB + 3) / 4;
+  double own0[R], own1[R];
+  int shift[R];
+  unsigned far = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    own0[r] = own1[r] = 1.0;
+    shift[r] = 0;
   }
 #pragma unroll
   for (int b = 0; b < MB; ++b) {
     const bool high = b >= MB - 2;
     const bool mine = high && ((q >> (b - (MB - 2))) & 1);    // the bit of all of this lane's labels
     int top[2] = {INT32_MIN, INT32_MIN};
-    float sum[2] = {0.0f, 0.0f};
+    double sum[2] = {0.0, 0.0};
 #pragma unroll
     for (int i = 0; i < P; ++i) top[high ? 0 : (i >> b) & 1] = max(top[high ? 0 : (i >> b) & 1], k[i]);
     if (high) {
@@ -232,29 +235,42 @@ __device__ __forceinline__ void rest_symbol(const float* x, int q, const float* 
 #pragma unroll
     for (int i = 0; i < P; ++i) {
       const int s = high ? 0 : (i >> b) & 1;
-      sum[s] += ldexpf(e[i], max(k[i] - (high ? ref : top[s]), -200));
+      sum[s] += ldexp(e[i], k[i] - (high ? ref : top[s]));
     }
     if (high) {
-      sum[1] = mine ? sum[0] : 0.0f;
-      sum[0] = mine ? 0.0f : sum[0];
+      sum[1] = mine ? sum[0] : 0.0;
+      sum[0] = mine ? 0.0 : sum[0];
     }
     sum[0] = quad_sum(sum[0]);
     sum[1] = quad_sum(sum[1]);
-    const float lg = fastk::kLn2 * (__builtin_amdgcn_logf(sum[0]) - __builtin_amdgcn_logf(sum[1]));
-    double L = static_cast<double>(top[0] - top[1]) * 0.69314718055994530942 + static_cast<double>(lg);
-    if (min(top[0], top[1]) < -1073741820) {
-      double m[2] = {INFINITY, INFINITY};
+    const bool keep = q == (b & 3);
+    own0[b >> 2] = keep ? sum[0] : own0[b >> 2];
+    own1[b >> 2] = keep ? sum[1] : own1[b >> 2];
+    shift[b >> 2] = keep ? top[0] - top[1] : shift[b >> 2];
+    far |= fp64::saturated(min(top[0], top[1])) ? 1u << b : 0u;
+    __builtin_amdgcn_sched_barrier(0);         // one bit's temporaries at a time (registers)
+  }
 #pragma unroll
-      for (int i = 0; i < P; ++i) {
-        const bool one = high ? mine : (i >> b) & 1;
-        m[0] = one ? m[0] : fmin(m[0], d2[i]);
-        m[1] = one ? fmin(m[1], d2[i]) : m[1];
-      }
-      m[0] = quad_min(m[0]);
-      m[1] = quad_min(m[1]);
-      // infinite points: no LLR
-      L = (m[0] < INFINITY && m[1] < INFINITY) ? cnat * (m[1] - m[0]) : __builtin_nan("");
+  for (int r = 0; r < R; ++r) {
+    const int b = 4 * r + q;
+    const double L = fma(static_cast<double>(shift[r]), fp64::kLn2, fp64::log_ratio<15, false>(own0[r], own1[r]));
+    if (b < MB) llr[n * MB + (MB - 1 - b)] = static_cast<float>(L);
+  }
+#pragma unroll 1
+  for (; far; far &= far - 1) {
+    const int b = __ffs(far) - 1;
+    double m[2] = {INFINITY, INFINITY};
+#pragma unroll 1
+    for (int i = 0; i < P; ++i) {
+      const bool one = ((q * P + i) >> b) & 1;
+      const double d2 = dist(i);
+      m[0] = one ? m[0] : fmin(m[0], d2);
+      m[1] = one ? fmin(m[1], d2) : m[1];
     }
+    m[0] = quad_min(m[0]);
+    m[1] = quad_min(m[1]);
+    // infinite points: no LLR
+    const double L = (m[0] < INFINITY && m[1] < INFINITY) ? cnat * (m[1] - m[0]) : __builtin_nan("");
     if (q == (b & 3)) llr[n * MB + (MB - 1 - b)] = static_cast<float>(L);
   }
 }
@@ -279,8 +295,11 @@ __global__ void __launch_bounds__(kVecThreads) llr_vec_rest_kernel(const float* 
     __syncthreads();
     const int count = list.count;
     if (threadIdx.x == 0 && count) atomicAdd(&flags[1], count);
-    for (int i = threadIdx.x / 4; i < count; i += kVecThreads / 4)
-      rest_symbol<MB, D>(pts + q * kStep, q, y, 64 * m0 + list.item[i], c, cnat, llr);
+    for (int i = threadIdx.x / 4; i < count; i += kVecThreads / 4) {
+      int at = q * kStep;                        // opaque: the points are read from LDS for every symbol (kept in
+      asm volatile("" : "+v"(at));               // registers they leave one wavefront a SIMD)
+      rest_symbol<MB, D>(pts + at, q, y, 64 * m0 + list.item[i], c, cnat, llr);
+    }
     __syncthreads();
   }
 }

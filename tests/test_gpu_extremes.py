@@ -3,8 +3,9 @@ leave the FP32 range: constellations and noise scaled by 1e20 and 1e-20, noise f
 points' distances, and symbols at equal distance from several points.
 
 Tolerances.  Factors of up to four points, and constellations of up to 16: those of test_gpu_product.py
-for M <= 16; other products: those of its FP32 distances; and 8 roundings of the farthest point's
-FP64 score, where scores cancel."""
+for M <= 16; other products: those of its FP32 distances; 32 and 64 points without structure, whose
+symbols all go to their FP64 pass here, the rounding of the result and 1e-9; and 8 roundings of the
+farthest point's FP64 score, where scores cancel."""
 import math
 
 import numpy as np
@@ -17,8 +18,17 @@ from test_gpu_product import pam, product, shape
 
 pytestmark = pytest.mark.gpu
 
+
+@pytest.fixture(scope="module", autouse=True)
+def forget_labels():
+    """Label buffers are checked on the host once per address: leave none behind."""
+    yield
+    import paper_2104_06311_amd as m
+    m.release_cache()
+
 DOUBLE = ["bpsk", "8psk", "gauss4", "gauss16", "qam4", "qam16", "2xqam16"]     # FP64 distances
 SINGLE = ["qam64", "qam256", "psk8x2", "rect32", "three", "planes256", "flat64", "quarter64"]   # some FP32
+GENERAL = ["gauss32", "gauss64"]
 
 
 def md():
@@ -27,14 +37,16 @@ def md():
 
 
 def points(name):
-    if name == "gauss4":                                   # one factor of four points
-        return synth.gaussian_constellation(4, 2, 4)
+    if name in ("gauss4", "gauss32", "gauss64"):           # gauss4: one factor of four points
+        return synth.gaussian_constellation(int(name[5:]), 2, 4)
     if name == "quarter64":                                # factors of four and of sixteen points
         return product(pam(4), pam(16))
     return shape(name)
 
 
 def bound(name):
+    if name in GENERAL:
+        return 1e-9, 2.0 ** -23
     if name in DOUBLE:
         return 4e-6, 2.0 ** -23
     return 3 * 2.0 ** -24 * 256 * math.log(2.0) + 4e-6, 4 * 2.0 ** -24
@@ -80,7 +92,16 @@ def test_scales(name, scale):
     assert np.all(np.abs(got - want) <= 1e-9 + 2.0 ** -23 * np.abs(want))
 
 
-@pytest.mark.parametrize("name", DOUBLE + SINGLE)
+@pytest.mark.parametrize("name", GENERAL)
+@pytest.mark.parametrize("scale", [1e20])
+def test_scales_without_structure(name, scale):
+    X, labels = points(name)
+    X = (X.astype(np.float64) * scale).astype(np.float32)
+    s2 = synth.sigma2_from_snr_db(X, 10.0)
+    check_exact(X, labels, received(X, s2, 517, 3), s2, *bound(name))
+
+
+@pytest.mark.parametrize("name", DOUBLE + SINGLE + GENERAL)
 @pytest.mark.parametrize("snr_db", [60.0, 100.0, 115.0, 200.0, 290.0])
 def test_little_noise(name, snr_db):
     X, labels = points(name)
@@ -131,3 +152,23 @@ def test_far_symbols_are_demapped_in_fp64(n, other, seed):
                        torch.tensor([[0.25, 0.0], [0.25, 1e3]], device="cuda"), 0.5)
     assert md().llr_path_counts() == (0, 0)
     assert np.all(np.abs(L.cpu().numpy()[:, :mf] - want) <= 2.0 ** -24 * np.abs(want) + 2e-12), (L[:, :mf], want)
+
+
+@pytest.mark.parametrize("M,D", [(32, 1), (64, 1), (64, 3), (32, 8)])
+@pytest.mark.parametrize("seed", range(3))
+def test_left_symbols_are_demapped_in_fp64(M, D, seed):
+    """The same without structure: the points with the highest label bit set are all out of reach."""
+    x, near = coinciding(M // 2, seed)
+    x, near = np.concatenate([x, 2e4 + np.arange(M // 2) ** 2]), np.concatenate([near, np.zeros(M // 2, bool)])
+    X = np.zeros((M, D), np.float32)
+    X[:, D - 1] = x
+    m = M.bit_length() - 1
+    k1 = (((np.arange(M)[:, None] >> np.arange(m - 2, -1, -1)) & 1) & near[:, None]).sum(0)
+    want = np.log((near.sum() - k1) / k1)
+    y = torch.zeros(70, D, device="cuda")
+    y[:, D - 1] = 0.25
+    L = md().llr_exact(torch.from_numpy(X).cuda(), torch.arange(M, dtype=torch.int32, device="cuda"), y, 0.5)
+    assert md().llr_path_counts() == (70, 0)
+    L = L.cpu().numpy()
+    assert np.all(np.abs(L[:, 1:] - want) <= 2.0 ** -24 * np.abs(want) + 2e-12), (L[0], want)
+    assert np.allclose(L[:, 0], (2e4 - 0.25) ** 2, rtol=1e-6)
