@@ -12,7 +12,7 @@ template <int MODE, bool GMI, int DT>
 __global__ void __launch_bounds__(kProdThreads) llr_prod_kernel(ProdArgs G, const int* __restrict__ flags, SymbolArgs A) {
   ConstInt* fl = reinterpret_cast<ConstInt*>(reinterpret_cast<uint64_t>(flags));
   if (!fl[5]) return;
-  all_symbols<MODE, GMI, DT>(G, flags, A);
+  all_symbols<MODE, GMI, DT, 0>(G, flags, A);
 }
 
 template <int MODE, bool GMI, int DT>

@@ -32,6 +32,7 @@
 #include "common.hpp"
 #include "fp64_form.hpp"
 #include "gmi_terms.hpp"
+#include "llr_kernels.hpp"
 
 namespace md {
 namespace prodk {
@@ -400,21 +401,31 @@ __device__ __forceinline__ void fixed_symbols(const ProdTables& T0, ConstInt* he
   if (some) *A.any_left = 1;
 }
 
-template <int MODE, int NF, int DF, bool GMI>
-__device__ __forceinline__ void fixed_shape(int mf, const ProdTables& T, ConstInt* head, const SymbolArgs& A) {
-  switch (mf) {
-    case 1: return fixed_symbols<MODE, 1, NF, DF, GMI>(T, head, A);
-    case 2: return fixed_symbols<MODE, 2, NF, DF, GMI>(T, head, A);
-    case 3: return fixed_symbols<MODE, 3, NF, DF, GMI>(T, head, A);
-    default: return fixed_symbols<MODE, 4, NF, DF, GMI>(T, head, A);
-  }
+// Whether constellations of m label bits in two or four coordinates come here: MB = 0, the product kernel
+// (M <= 16 exact; products of 128 to kProdMaxM points; max-log both), or the kernel for 2^MB points.
+template <int MODE, int MB>
+constexpr bool comes_here(int m) {
+  if (MB != 0) return m == MB;
+  return (MODE != PROD_FLOAT && (1 << m) <= kSmallM) || (MODE != PROD_DOUBLE && m >= 7 && (1 << m) <= kProdMaxM);
+}
+
+// False: no loop of its own for this shape.
+template <int MODE, int NF, int DF, bool GMI, int MB, int MF = 1>
+__device__ __forceinline__ bool fixed_shape(int mf, const ProdTables& T, ConstInt* head, const SymbolArgs& A) {
+  if constexpr (comes_here<MODE, MB>(NF * MF))
+    if (mf == MF) {
+      fixed_symbols<MODE, MF, NF, DF, GMI>(T, head, A);
+      return true;
+    }
+  if constexpr (MF < kProdMaxBits) return fixed_shape<MODE, NF, DF, GMI, MB, MF + 1>(mf, T, head, A);
+  return false;
 }
 
 // GMI: also the loss term of every symbol (NaN for a transmitted index outside the labels).
 // DT = 2 and 4: the even shapes of two and four coordinates (QAM; its 4D products, and those of
 // planes; 2D constellations of up to 16 points) take the loop above, everything else the general
 // one.
-template <int MODE, bool GMI, int DT>
+template <int MODE, bool GMI, int DT, int MB>
 __device__ __forceinline__ void all_symbols(const ProdArgs& G, const int* __restrict__ flags, SymbolArgs A) {
   ConstInt* fl = reinterpret_cast<ConstInt*>(reinterpret_cast<uint64_t>(flags));
   A.start = fl[0] != 0 ? __builtin_nanf("") : 0.0f;
@@ -433,12 +444,11 @@ __device__ __forceinline__ void all_symbols(const ProdArgs& G, const int* __rest
     for (int f = 0; f < nf; ++f)
       even = even && head[kProdHead + kProdFactor * f] == mf && head[kProdHead + kProdFactor * f + 1] * nf == DT;
     if constexpr (DT == 2) {
-      if (even && nf == 2) return fixed_shape<MODE, 2, 1, GMI>(mf, T, head, A);
-      if constexpr (MODE != PROD_FLOAT)
-        if (even && nf == 1) return fixed_shape<MODE, 1, 2, GMI>(mf, T, head, A);
+      if (even && nf == 2 && fixed_shape<MODE, 2, 1, GMI, MB>(mf, T, head, A)) return;
+      if (even && nf == 1 && fixed_shape<MODE, 1, 2, GMI, MB>(mf, T, head, A)) return;
     } else {
-      if (even && nf == 4) return fixed_shape<MODE, 4, 1, GMI>(mf, T, head, A);
-      if (even && nf == 2) return fixed_shape<MODE, 2, 2, GMI>(mf, T, head, A);
+      if (even && nf == 4 && fixed_shape<MODE, 4, 1, GMI, MB>(mf, T, head, A)) return;
+      if (even && nf == 2 && fixed_shape<MODE, 2, 2, GMI, MB>(mf, T, head, A)) return;
     }
   }
   const int64_t stride = static_cast<int64_t>(gridDim.x) * kProdThreads;

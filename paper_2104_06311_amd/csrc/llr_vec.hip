@@ -45,7 +45,7 @@ __global__ void __launch_bounds__(kVecThreads) llr_vec_kernel(const float* __res
   // a product constellation: by its factors (a launch less than a kernel of its own)
   if (flags[5]) {
     constexpr int mode = MAXLOG ? prodk::PROD_MAXLOG : prodk::PROD_FLOAT;
-    return prodk::all_symbols<mode, GMI, (D == 2 || D == 4) ? D : 0>(G, flags, A);
+    return prodk::all_symbols<mode, GMI, (MB == 6 && (D == 2 || D == 4)) ? D : 0, MB>(G, flags, A);
   }
   typedef const __attribute__((address_space(4))) float ConstFloat;
   const bool invalid = flags[0] != 0;
