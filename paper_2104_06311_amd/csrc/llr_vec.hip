@@ -64,6 +64,7 @@ __global__ void __launch_bounds__(kVecThreads) llr_vec_kernel(const float* __res
       yv[d] = y[n * D + d];
       ysq = fmaf(yv[d], yv[d], ysq);
     }
+    const bool nan_y = ysq != ysq;
     // max-log takes differences of scores only: the terms common to all points (the bias
     // and -c ||y||^2) drop out, and leaving them out keeps the scores' magnitude small
     const float r = MAXLOG ? 0.0f : fmaf(-c, ysq, fastk::kExpBias);
@@ -103,7 +104,9 @@ __global__ void __launch_bounds__(kVecThreads) llr_vec_kernel(const float* __res
     // the wavefront's symbols left to the kernel below, one bit each (its 64 symbols are one
     // aligned run); an append to a common list, one atomic per wavefront that has any, took 190 us
     // at 1e6 symbols where a tenth of them is out of range
-    const bool out = !invalid && !fastk::sums_in_range<MB>(S0, S1);
+    // (a NaN sum of a received value that is none: an operand outside the FP32 range)
+    const float all = S0[0] + S1[0];
+    const bool out = !invalid && (!fastk::sums_in_range<MB>(S0, S1) || (all != all && !nan_y));
     const uint64_t mask = __ballot(out);
     if ((n & 63) == 0) left[n >> 6] = mask;
     if (invalid) {

@@ -397,7 +397,7 @@ __global__ void __launch_bounds__(kOneThreads) prep_one_kernel(const float* __re
     }
     if (vx) {
       // the vector demapper's terms (M <= 64, resident): 2c x (D floats) and -c ||x||^2, FP32 as
-      // it computes
+      // it computes; NaN where that overflows, so that no sum misses the point unnoticed
       const float c = c_over_alpha * alpha;
       for (int s = tid; s < M; s += nt) {
         float n32 = 0.0f;
@@ -406,7 +406,7 @@ __global__ void __launch_bounds__(kOneThreads) prep_one_kernel(const float* __re
           vx[s * (D + 1) + d] = 2.0f * c * v;
           n32 = fmaf(v, v, n32);
         }
-        vx[s * (D + 1) + D] = -c * n32;
+        vx[s * (D + 1) + D] = c * n32 < INFINITY ? -c * n32 : __builtin_nanf("");
       }
     }
     if (bad) sh_bad = 1;

@@ -93,7 +93,7 @@ def test_scales(name, scale):
 
 
 @pytest.mark.parametrize("name", GENERAL)
-@pytest.mark.parametrize("scale", [1e20])
+@pytest.mark.parametrize("scale", [1e20, 1e19, 1e-20])
 def test_scales_without_structure(name, scale):
     X, labels = points(name)
     X = (X.astype(np.float64) * scale).astype(np.float32)
