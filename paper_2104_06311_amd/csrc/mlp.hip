@@ -747,6 +747,7 @@ int ensure_scratch(Mlp* p, size_t floats) {
     MD_HIP_TRY(md::dev_free(p->scratch));
     p->scratch = nullptr;
     p->scratch_cap = 0;
+    p->pack_version = -1;      // the copies are gone, whether or not the allocation below succeeds
   }
   void* q = nullptr;
   if (md::dev_malloc(&q, floats * sizeof(float)) != hipSuccess) {
@@ -755,7 +756,6 @@ int ensure_scratch(Mlp* p, size_t floats) {
   }
   p->scratch = static_cast<float*>(q);
   p->scratch_cap = floats;
-  p->pack_version = -1;
   return MD_OK;
 }
 
