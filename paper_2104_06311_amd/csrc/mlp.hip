@@ -724,7 +724,7 @@ struct Mlp {
   int64_t pack_version = -1;   // version whose BF16 training copies `scratch` holds, -1: none
   bool captured = false;       // training work of this handle was captured into a graph: its
                                // replays change parameters unseen, so the copies are made anew
-                               // by every gradient
+                               // by every gradient, and the image by every inference
 };
 
 namespace {
@@ -788,10 +788,16 @@ int colsum(const float* G, int64_t B, int n, float* partial, float* out, hipStre
   return MD_OK;
 }
 
-int note_capture(Mlp* p, hipStream_t s) {
+int is_capturing(hipStream_t s, bool* capturing) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   MD_HIP_TRY(hipStreamIsCapturing(s, &cap));
-  if (cap != hipStreamCaptureStatusNone) p->captured = true;
+  *capturing = cap != hipStreamCaptureStatusNone;
+  return MD_OK;
+}
+int note_capture(Mlp* p, hipStream_t s) {
+  bool capturing = false;
+  MD_TRY(is_capturing(s, &capturing));
+  p->captured = p->captured || capturing;
   return MD_OK;
 }
 
@@ -998,10 +1004,14 @@ int infer(Mlp* p, const float* d_y, int64_t N, float* d_llr, hipStream_t s) {
     }
     p->img = static_cast<char*>(q);
   }
-  if (p->img_version != p->version) {
+  // Under capture the image is packed by the captured work itself (parameters may change between its
+  // replays), and nothing is packed yet when this returns.
+  bool capturing = false;
+  if (const int st = is_capturing(s, &capturing); st != MD_OK) return st;
+  if (capturing || p->captured || p->img_version != p->version) {
     hipLaunchKernelGGL(pack_infer_kernel, dim3(256), dim3(256), 0, s, p->w, p->D, p->H, p->m, L, p->img);
     MD_LAUNCH_CHECK("pack_infer_kernel launch");
-    p->img_version = p->version;
+    p->img_version = capturing ? -1 : p->version;
   }
   if (fused) {
     switch (L.nrb) {
