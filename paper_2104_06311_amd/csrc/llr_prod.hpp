@@ -117,7 +117,8 @@ __device__ __forceinline__ void subset_min(const R (&d2)[1 << MF], int b, R* m0,
 template <int MF, bool LOG64>
 __device__ __forceinline__ float subset_llr(const double (&d2)[1 << MF], int b, double c, double cnat, double (&mn)[2]) {
   subset_min<MF>(d2, b, &mn[0], &mn[1]);
-  if constexpr (MF == 1) return static_cast<float>(cnat * (mn[1] - mn[0]));
+  // (a point that is not finite, M = 2: NaN, as a sum of its terms would be)
+  if constexpr (MF == 1) return static_cast<float>(fma(cnat, mn[1] - mn[0], 0.0 * (mn[0] + mn[1])));
   float s[2] = {0.0f, 0.0f};
   if constexpr (MF == 2) {
 #pragma unroll
@@ -183,7 +184,8 @@ __device__ __forceinline__ void llr_from_distances(const Real<MODE, MF> (&d2)[1 
     for (int b = 0; b < MF; ++b) {
       double m0, m1;
       subset_min<MF>(d2, b, &m0, &m1);
-      L[b] = static_cast<float>(cnat * (m1 - m0));
+      // (NaN points are left out, also when a subset has no others: infinitely far)
+      L[b] = static_cast<float>(cnat * (fmin(m1, INFINITY) - fmin(m0, INFINITY)));
     }
   } else if constexpr (!kFloat<MODE, MF>) {
     double near = 0.0, far = 0.0;
