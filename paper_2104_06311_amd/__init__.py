@@ -18,12 +18,19 @@ __all__ = ["awgn_sample", "llr_exact", "llr_exact_noalloc", "llr_exact_gmi", "gm
            "log2_exact"]
 
 
+# The direct way to the current stream's handle is private to torch: used where it is there.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    """Handle of torch's current stream (asked for directly: building torch's stream object for it
-    took 2.9 us of every call, this 0.3)."""
+    """Handle of torch's current stream (asked for directly where torch allows: building torch's stream
+    object for it took 2.9 us of every call, this 0.3)."""
+    if _raw_stream is None or _raw_device is None:
+        return torch.cuda.current_stream().cuda_stream
     if not torch.cuda.is_initialized():
         torch.cuda.init()
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(_raw_device())
 
 
 def _ptr(t):
