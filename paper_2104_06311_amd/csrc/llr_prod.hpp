@@ -69,28 +69,48 @@ struct ProdTables {
 __device__ __forceinline__ double min_r(double a, double b) { return fmin(a, b); }
 __device__ __forceinline__ float min_r(float a, float b) { return fminf(a, b); }
 
-// Squared distances of the group's points; `nonfinite` collects 0 * y (NaN for inf and NaN).
+// Squared distances of the group's points; `nonfinite` collects 0 * y (NaN for inf and NaN).  Groups of
+// two and four points take several coordinates at a time: one by one each waited for its index, then
+// for its points (M = 2, D = 30, 1000 symbols: 29 us a call, 25 so).
 template <int MF, class R>
 __device__ __forceinline__ void distances(const ProdTables& T, const float* __restrict__ row, R (&d2)[1 << MF],
                                           float* nonfinite) {
+  constexpr int U = MF == 1 ? 8 : (MF == 2 ? 4 : 1);
   const int df = T.fd[1];
-  auto coord = [&](int i, auto first) {
-    const int co = T.fd[8 + i];
-    const float yf = row[co];
-    *nonfinite = fmaf(yf, 0.0f, *nonfinite);
-    const R y = static_cast<R>(yf);
+  auto coords = [&](int i, auto first, auto count) {
+    constexpr int C = decltype(count)::value;
+    int co[C];
+    float yf[C];
+    R x[C][1 << MF];
 #pragma unroll
-    for (int p = 0; p < (1 << MF); ++p) {
-      R x;
-      if constexpr (sizeof(R) == 8) x = T.td[16 * co + p];
-      else x = T.tf[16 * co + p];
-      const R diff = y - x;
-      if constexpr (decltype(first)::value) d2[p] = diff * diff;
-      else d2[p] = fma(diff, diff, d2[p]);
+    for (int u = 0; u < C; ++u) co[u] = T.fd[8 + i + u];
+#pragma unroll
+    for (int u = 0; u < C; ++u) {
+      yf[u] = row[co[u]];
+#pragma unroll
+      for (int p = 0; p < (1 << MF); ++p) {
+        if constexpr (sizeof(R) == 8) x[u][p] = T.td[16 * co[u] + p];
+        else x[u][p] = T.tf[16 * co[u] + p];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < C; ++u) {
+      *nonfinite = fmaf(yf[u], 0.0f, *nonfinite);
+      const R y = static_cast<R>(yf[u]);
+#pragma unroll
+      for (int p = 0; p < (1 << MF); ++p) {
+        const R diff = y - x[u][p];
+        if (decltype(first)::value && u == 0) d2[p] = diff * diff;
+        else d2[p] = fma(diff, diff, d2[p]);
+      }
     }
   };
-  coord(0, std::true_type{});
-  for (int i = 1; i < df; ++i) coord(i, std::false_type{});
+  typedef std::integral_constant<int, 1> One;
+  coords(0, std::true_type{}, One{});
+  int i = 1;
+  if constexpr (U > 1)
+    for (; i + U <= df; i += U) coords(i, std::false_type{}, std::integral_constant<int, U>{});
+  for (; i < df; ++i) coords(i, std::false_type{}, One{});
 }
 
 // Smallest distance of the label-0 and label-1 subset of bit b.

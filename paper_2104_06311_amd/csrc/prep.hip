@@ -371,23 +371,34 @@ __global__ void __launch_bounds__(kOneThreads) prep_one_kernel(const float* __re
     for (int attempt = 0; prod && !product && attempt < 2; ++attempt) {
       if (!guess_groups(pts, G, tab, magic, magic_m, attempt == 1)) break;
       bool differs = false;
+      // place of the bits mk of label l among themselves
+      auto compact = [](uint32_t l, uint32_t mk) {
+        uint32_t p = 0;
+        for (int i = 0; mk; ++i, mk &= mk - 1) p |= ((l >> (__ffs(mk) - 1)) & 1u) << i;
+        return p;
+      };
+      auto check = [&](int l, int d, uint32_t p) {
+        const float v = pts(l, d);
+        differs |= !(fabsf(v) < INFINITY) || v != tab[16 * d + p];
+      };
+      if (attempt == 0 && M < nt) {
+        // a thread per point and coordinate (coordinate by coordinate, as below, 30 of them took 10 us)
 #pragma unroll 1
-      for (int d = 0; attempt == 0 && d < D; ++d) {
-        const int f = __builtin_amdgcn_readfirstlane(G.of[d]);
-        const uint32_t mk = f >= 0 ? __builtin_amdgcn_readfirstlane(G.comp[f]) : 0u;
-        const uint32_t low = mk & (0u - mk);
-        const int shift = mk ? __ffs(mk) - 1 : 0;
-        const bool run = (mk & (mk + low)) == 0;       // consecutive bits: a shift and a mask
+        for (int e = tid; e < M * D; e += nt) {
+          const int l = div_by(e, magic), d = e - l * D;
+          const int f = G.of[d];
+          check(l, d, compact(l, f >= 0 ? G.comp[f] : 0u));
+        }
+      } else {
+#pragma unroll 1
+        for (int d = 0; attempt == 0 && d < D; ++d) {
+          const int f = __builtin_amdgcn_readfirstlane(G.of[d]);
+          const uint32_t mk = f >= 0 ? __builtin_amdgcn_readfirstlane(G.comp[f]) : 0u;
+          const uint32_t low = mk & (0u - mk);
+          const int shift = mk ? __ffs(mk) - 1 : 0;
+          const bool run = (mk & (mk + low)) == 0;       // consecutive bits: a shift and a mask
 #pragma unroll 4
-        for (int l = tid; l < M; l += nt) {
-          uint32_t p = (static_cast<uint32_t>(l) & mk) >> shift;
-          if (!run) {
-            p = 0;
-            uint32_t left = mk;
-            for (int i = 0; left; ++i, left &= left - 1) p |= ((static_cast<uint32_t>(l) >> (__ffs(left) - 1)) & 1u) << i;
-          }
-          const float v = pts(l, d);
-          differs |= !(fabsf(v) < INFINITY) || v != tab[16 * d + p];
+          for (int l = tid; l < M; l += nt) check(l, d, run ? (static_cast<uint32_t>(l) & mk) >> shift : compact(l, mk));
         }
       }
       if (differs) sh_differs = 1;
