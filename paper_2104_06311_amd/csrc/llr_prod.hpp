@@ -452,9 +452,9 @@ __device__ __forceinline__ void all_symbols(const ProdArgs& G, const int* __rest
   ConstInt* fl = reinterpret_cast<ConstInt*>(reinterpret_cast<uint64_t>(flags));
   A.start = fl[0] != 0 ? __builtin_nanf("") : 0.0f;
   // The FP32 form: while an FP32 squared distance that overflows means a score of 2^28 and more, and
-  // one that underflows a score below 2^-28; and not for constellations the general path would
-  // leave to its FP64 kernel (flags[2]).
-  A.fp32_ok = A.c >= 1e-30 && A.c <= 1e30 && fl[2] == 0;
+  // one that underflows a score below 2^-28; and, from 128 points on, not for constellations the
+  // general path would leave to its FP64 kernel (flags[2]).
+  A.fp32_ok = A.c >= 1e-30 && A.c <= 1e30 && (MB != 0 || fl[2] == 0);
   ConstInt* head = reinterpret_cast<ConstInt*>(reinterpret_cast<uint64_t>(G.prod));
   ProdTables T;
   T.td = reinterpret_cast<ConstDouble*>(reinterpret_cast<uint64_t>(G.ptab));
