@@ -10,8 +10,9 @@
 // Per group and symbol: squared distances of its 2^MF <= 16 points in difference form, then
 //   max-log:              L_b = cnat (min_{b=1} d2 - min_{b=0} d2), FP64 distances;
 //   exact, M <= 16, and groups of up to 4 points: FP64 distances; per label subset the smallest
-//     (FP64) and the FP32 sum of 2^-(c (d2 - min)), L_b = cnat (min1 - min0) + ln (sum0 / sum1); the
-//     logarithm in FP64, but for the 4-point groups of larger constellations in two and four dimensions;
+//     (FP64) and the FP32 sum of 2^-(c (d2 - min)), L_b = cnat (min1 - min0) + ln (sum0 / sum1), the
+//     logarithm in FP64 for M <= 16 (not for 4-point groups of products in two and four dimensions, see
+//     subset_llr);
 //   exact, 8 and 16 points of M >= 32 (where the general path's scores are FP32): FP32
 //     distances, one exponential per point relative to the nearest, the subset sums by a tree,
 //     L_b = ln (S0 / S1).  A bit whose smaller sum fell below 2^-100 takes its subsets' smallest
@@ -24,7 +25,7 @@
 // Bound by memory for up to 4 points a factor (4e6 symbols of 16-QAM, a whole call: 207.7 ->
 // 26.9 us, 3.6e12 B/s of its 24 bytes a symbol) and by vector instructions, about 4.4 cycles
 // each, for 16 (1e6 symbols of 256-QAM: 71.3 -> 36.9 us).  LLRs are no further from 64-bit ones
-// than before (relative 2-norm 2.5e-8 and 5.3e-8 against 2.5e-8 and 2.6e-7).
+// than before (relative 2-norm 2.5e-8 and 5.7e-8 against 2.5e-8 and 2.6e-7).
 #pragma once
 
 #include <type_traits>
@@ -129,10 +130,11 @@ __device__ __forceinline__ void subset_min(const R (&d2)[1 << MF], int b, R* m0,
 // scaled in FP64 and rounded last: neither they nor c need lie in the FP32 range, and the smallest
 // distance's own term is 1 however large c times it is.
 //
-// LOG64: the logarithm in FP64 (some 17 instructions; its 1e-10 is far below the sums' 6e-8).  FP32 logarithms add about what two FP32 sums carry: 8-PSK at 2 dB 3.34e-8
-// (relative 2-norm) against 3.24e-8, an unstructured M = 4 at -4 dB 5.98e-8 against 5.33e-8; but they
-// take 26 us of 4e6 16-QAM symbols where FP64 ones take 34, and the sums of a 4-point group are of
-// two terms instead of 8: 3.30e-8 at 2 dB, 3.90e-8 over all 16 points with FP64 logarithms.
+// LOG64: the logarithm in FP64 (some 17 instructions; its 1e-10 is far below the sums' 6e-8).  FP32
+// logarithms add about what two FP32 sums carry: 8-PSK at 2 dB 3.34e-8 (relative 2-norm) against 3.24e-8,
+// an unstructured M = 4 at -4 dB 5.98e-8 against 5.33e-8; but they take 26 us of 4e6 16-QAM symbols where
+// FP64 ones take 34, and the sums of a 4-point group are of two terms instead of 8: 3.30e-8 at 2 dB,
+// 3.90e-8 over all 16 points with FP64 logarithms.
 // mn: the subsets' smallest distances.
 template <int MF, bool LOG64>
 __device__ __forceinline__ float subset_llr(const double (&d2)[1 << MF], int b, double c, double cnat, double (&mn)[2]) {
@@ -175,20 +177,21 @@ struct Reach {
 __device__ __forceinline__ bool in_range(const Reach& r) { return r.top <= 256.0f && r.top + r.beyond <= 575.0f; }
 
 // The LLR of bit b when one of its sums is too small: FP64 smallest distances (dist64(p): the
-// distance of point p), FP32 sums relative to the FP32 ones.
+// distance of point p), FP32 sums relative to the FP32 ones (rounded scores: good within in_range).
 template <int MF, class F>
 __device__ __forceinline__ float wide_llr(const float (&d2)[1 << MF], int b, float cf, double cnat, F dist64, float top,
                                           Reach& reach) {
   float mf[2];
   subset_min<MF>(d2, b, &mf[0], &mf[1]);
-  reach.beyond = fmaxf(reach.beyond, cf * fmaxf(mf[0], mf[1]) - top);
+  const float cm[2] = {cf * mf[0], cf * mf[1]};
+  reach.beyond = fmaxf(reach.beyond, fmaxf(cm[0], cm[1]) - top);
   double mn[2] = {INFINITY, INFINITY};
   float s[2] = {0.0f, 0.0f};
 #pragma unroll
   for (int p = 0; p < (1 << MF); ++p) {
     const int v = (p >> b) & 1;
     mn[v] = fmin(mn[v], dist64(p));
-    s[v] += __builtin_amdgcn_exp2f(cf * (mf[v] - d2[p]));
+    s[v] += __builtin_amdgcn_exp2f(fmaf(-cf, d2[p], cm[v]));
   }
   const float lg = kLn2f * (__builtin_amdgcn_logf(s[0]) - __builtin_amdgcn_logf(s[1]));
   return static_cast<float>(cnat * (mn[1] - mn[0]) + static_cast<double>(lg));
