@@ -142,7 +142,13 @@ int awgn_sample(const float* d_X, int M, int D, uint64_t seed, uint64_t offset, 
  * two exponent windows (down to 386 units), what those miss in three (576 units), and
  * what is still left by a per-subset-maximum FP64 evaluation, so every finite input
  * gives finite LLRs (llr_path_counts reports how many symbols took each stage).  M = 32 and
- * 64 with D <= 8 have one such pass, with FP64 distances and no limit to its range.
+ * 64 with D <= 8 have one such pass, FP64 throughout and with no limit to its range.
+ * Precision of MD_PREC_FP32: scores and sums FP32 in the first pass and the exponent windows, FP64
+ * throughout after them.  M <= 16: FP64 distances, FP32 exponentials and sums, FP64 logarithms
+ * (FP32 for groups of 4 points of a larger product in two and four dimensions).  Products of 32
+ * points and more: FP64 distances in groups of up to 4 points, FP32 in larger ones, FP32 sums; symbols
+ * that reach more than 575 base-2 units, and calls whose c = log2(e) / (2 sigma2) is outside
+ * 1e-30 .. 1e30 or (M >= 128) whose points are outside the split-FP16 range, FP64 throughout.
  * Returns MD_OK (N = 0 enqueues nothing), MD_EINVAL, MD_ENOTPOW2, MD_ELABEL,
  * MD_EDIM, MD_ENOMEM, MD_EHIP. */
 int llr_exact(const float* d_X, const uint32_t* d_labels, int M, int D, const float* d_y,

@@ -121,7 +121,8 @@ struct Prepared {
                             // [4] third fallback count, [5] the product kernel takes the call,
                             // [6] it left symbols (8 ints)
   unsigned* fb_list;        // symbols the fast pass could not finish (capacity N); after the
-                            // second pass it is reused for the third list (careful kernel)
+                            // second pass it is reused for the third list (careful kernel);
+                            // one bit per symbol where the vector or the product kernel ran
   unsigned* fb_list2;       // symbols left after the two-window pass (capacity N)
   int ks;                   // number of 16-slot K steps of the fragment
   int sc;                   // score contraction: 0 split FP16, 1 one FP16 pass, 2 one BF16 pass
@@ -145,8 +146,9 @@ struct Prepared {
 
 // Layout of Prepared::prod.  [0] factors, [1] coordinates equal for every point, [2 ..] those
 // coordinates; factor f at kProdHead + kProdFactor f: [0] label bits, [1] coordinates, [3 + i]
-// LLR column of its bit i, [7] whether those columns are consecutive, [8 ..] its coordinates.  Point p of a factor is the one whose label
-// bits are p's and whose other label bits are zero; ptab[16 d + p] is its coordinate d.
+// LLR column of its bit i, [7] whether those columns are consecutive, [8 ..] its coordinates.
+// Point p of a factor is the one whose label bits are p's and whose other label bits are zero;
+// ptab[16 d + p] is its coordinate d.
 constexpr int kProdMaxBits = 4;      // label bits of a factor
 constexpr int kProdHead = 32;
 constexpr int kProdFactor = 40;
@@ -158,8 +160,8 @@ constexpr int kSmallM = 16;          // constellations that one factor always ho
 size_t prep_bytes(int M, int D, int64_t N);   // an upper bound for every fragment layout
 // `flags` (8 ints) may be given by the caller; otherwise they are carved from ws.
 // sc selects the fragment layout of the score contraction (Prepared::sc); product: look for
-// the factors of a product constellation (M <= 8192; callers: product_rule) and let the product kernel take the call
-// when there are some (always for M <= kSmallM, which then needs no fragments).
+// the factors of a product constellation (callers: product_rule) and let the product kernel take the
+// call when there are some (always for M <= kSmallM, which then needs no fragments).
 int prepare(const float* d_X, const uint32_t* d_labels, int M, int D, int64_t N, float alpha,
             float c_over_alpha, char* ws, hipStream_t stream, Prepared* out, int* flags = nullptr, int sc = 0,
             bool product = false);

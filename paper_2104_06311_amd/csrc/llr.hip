@@ -2,10 +2,12 @@
 //
 // Product constellations (llr_prod.hip): when the label bits and coordinates of a constellation
 // fall into independent groups of up to 16 points, found and verified by prep on every call,
-// every symbol is demapped group by group, and the kernels below return at once.  The line: the
+// every symbol is demapped group by group, and the kernels below return at once, but for the
+// careful one, which finishes the symbols that reach too far for FP32 sums.  The line: the
 // exponentials and additions of a symbol go from M to the sum of the groups' points, so every
 // such constellation gains from M = 32 on (64 -> 16 points for 4D M = 64), but for the launch of
-// the kernel that finds nothing to do; the upper end is explained at product_rule.  M <= 16 always takes that kernel (one group if no more).
+// the kernel that finds nothing to do; the upper end is explained at product_rule.  M <= 16 always
+// takes that kernel (one group if no more).
 // Reduced-precision scores (FP16, BF16) of M >= 32 keep the general path, whose rounding is what
 // their caller asked for.
 //

@@ -12,8 +12,8 @@ int launch_awgn(const float* d_X, int M, int D, uint64_t seed, uint64_t offset, 
 // contraction, and c / a with c = log2(e) / (2 sigma2).
 void score_scales(double sigma2, float* alpha, float* c_over_alpha);
 
-// Fast MFMA path (M >= 32) followed by the careful kernel on the fallback list, or the
-// careful kernel on every symbol (M < 32).
+// Product kernel (M <= 16, and where prepare looked for factors), vector kernel (M = 32 and 64, D <= 8) or
+// matrix-core path, each followed by the passes for the symbols it left.
 int launch_llr(const Prepared& P, int M, int D, const float* d_y, int64_t N, double sigma2, bool maxlog,
                int prec, float* d_llr, hipStream_t stream);
 int launch_fast_exact(const Prepared& P, int M, int D, const float* d_y, int64_t N, double sigma2, float* d_llr,
@@ -38,7 +38,8 @@ bool vec_exact_supported(int M, int D);
 int launch_vec_exact(const Prepared& P, int M, int D, const float* d_y, int64_t N, double sigma2, float* d_llr,
                      hipStream_t stream, bool maxlog = false);
 // LLRs from the factors prepare() found (P.prod): the kernel returns at once when they are
-// none (flags[5] clear), and the general kernels return at once when there are some.
+// none (flags[5] clear), and the general kernels return at once when there are some, but for the last
+// one, which finishes the symbols that the product kernel marked (P.fb_list: one bit per symbol).
 int launch_prod(const Prepared& P, int M, int D, const float* d_y, int64_t N, double sigma2, bool maxlog,
                 float* d_llr, hipStream_t stream);
 // Whether a call looks for factors: every call with M <= kSmallM, and up to kProdMaxM points the

@@ -149,7 +149,7 @@ __device__ __forceinline__ int64_t frag_index(int s, int KS, int g) {
 // flipped) of a few base labels; the groups they give are then verified on every point, with
 // exact comparison (prep_one_kernel), so a wrong guess can only say "no product".  Up to 16
 // points a group; with M <= kSmallM the whole constellation is one group if nothing else.
-struct Groups {
+struct FactorGroups {
   uint32_t dep[32], comp[16];    // label bits a coordinate depends on; label bits of a group
   int of[32], rank[32];          // group of a coordinate (-1: equal for every point), its place there
   int size[32];                  // coordinates of its group
@@ -175,7 +175,7 @@ struct Points {
 
 // The groups, and tab[16 d + p]: coordinate d of its group's point p.  Called by every thread
 // of one block; false: no product.
-__device__ bool guess_groups(const Points& x, Groups& G, float* __restrict__ tab, uint32_t magic_d, uint32_t magic_m,
+__device__ bool guess_groups(const Points& x, FactorGroups& G, float* __restrict__ tab, uint32_t magic_d, uint32_t magic_m,
                              bool one_group) {
   constexpr int kBases = 8;
   const int M = x.M, D = x.D;
@@ -252,7 +252,7 @@ __device__ bool guess_groups(const Points& x, Groups& G, float* __restrict__ tab
 }
 
 // Writes the factors (layout in common.hpp).
-__device__ void write_groups(const Groups& G, const float* __restrict__ tab, int M, int D, int* __restrict__ prod,
+__device__ void write_groups(const FactorGroups& G, const float* __restrict__ tab, int M, int D, int* __restrict__ prod,
                              double* __restrict__ ptab, float* __restrict__ ptabf) {
   const int tid = threadIdx.x, nt = blockDim.x;
   const int m = 31 - __clz(M);
@@ -315,7 +315,7 @@ __global__ void __launch_bounds__(kOneThreads) prep_one_kernel(const float* __re
                                                                float* __restrict__ ptabf) {
   extern __shared__ uint32_t inv[];          // M entries; block 0: 16 D floats of factor points, the stage
   __shared__ int sh_bad, sh_range, sh_differs;
-  __shared__ Groups G;
+  __shared__ FactorGroups G;
   const int tid = threadIdx.x, nt = blockDim.x;
   float* tab = reinterpret_cast<float*>(inv + M);
   float* xs = tab + 16 * D;
