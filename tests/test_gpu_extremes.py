@@ -169,3 +169,49 @@ def test_left_symbols_are_demapped_in_fp64(M, D, seed):
     L = L.cpu().numpy()
     assert np.all(np.abs(L[:, 1:] - want) <= 2.0 ** -24 * np.abs(want) + 2e-12), (L[0], want)
     assert np.allclose(L[:, 0], (2e4 - 0.25) ** 2, rtol=1e-6)
+
+
+@pytest.mark.parametrize("name", ["qam64", "qam256", "2xqam16", "planes256", "gauss64"])
+@pytest.mark.parametrize("snr_db", [16.0, 24.0, 27.0, 40.0])
+def test_fused_gmi_takes_left_symbols_from_their_llrs(name, snr_db):
+    """None, some and all symbols left: the fused loss terms against gmi_reduce of the same LLRs.  A term is
+    2^-22 of itself and of its LLRs' rounding (2^-24 of up to 1e4 here, where it is not near zero) off."""
+    X, labels = points(name)
+    s2 = synth.sigma2_from_snr_db(X, snr_db)
+    Xd, ld = torch.from_numpy(X).cuda(), torch.from_numpy(labels.astype(np.int32)).cuda()
+    tx, y = md().awgn_sample(Xd, 11, 0, 70001, math.sqrt(s2))
+    tx[:50] = (tx[:50] + 1) % len(X)                        # some wrong ones, so that terms are large
+    L, g, se = md().llr_exact_gmi(Xd, ld, y, tx, s2)
+    assert torch.equal(L, md().llr_exact(Xd, ld, y, s2))
+    G, _, SE = md().gmi_reduce(L, tx, ld)
+    loss = (len(labels).bit_length() - 1) - G.item()
+    assert abs(g.item() - G.item()) <= 2e-6 * (loss + 1.0) and abs(se.item() - SE.item()) <= 1e-4 * SE.item()
+
+
+@pytest.mark.parametrize("name", ["qam64", "qam256"])
+def test_captured_calls_with_and_without_left_symbols(name):
+    """One graph replayed with received values of which some, then none, then all are left."""
+    X, labels = points(name)
+    s2 = synth.sigma2_from_snr_db(X, 25.0)
+    Xd, ld = torch.from_numpy(X).cuda(), torch.from_numpy(labels.astype(np.int32)).cuda()
+    m = len(labels).bit_length() - 1
+    rng = np.random.default_rng(8)
+    near = X[np.argsort((X ** 2).sum(1))[:4]]               # next to the axes: no far subset
+    some = X[rng.integers(0, len(X), 3000)]
+    ys = [some, near[rng.integers(0, 4, 3000)] * 0.2, 40.0 * some, some]
+    ys = [torch.from_numpy((v + math.sqrt(s2) * rng.standard_normal(v.shape)).astype(np.float32)).cuda() for v in ys]
+    y, out = torch.empty_like(ys[0]), torch.empty(3000, m, device="cuda")
+    y.copy_(ys[0])
+    md().llr_exact_noalloc(Xd, ld, y, s2, out=out)          # looks the array's address up
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        md().llr_exact_noalloc(Xd, ld, y, s2, out=out)
+    for v in ys:
+        want = md().llr_exact(Xd, ld, v, s2)
+        y.copy_(v)
+        out.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
